@@ -457,8 +457,8 @@ def decode(H, W, E, radices, K, itemset=None, buffers=None, stream=None, U=None,
         parts = user_projection_levels(H, W, radices, buffers.user_parts, stream=stream)
     if level_events is not None:
         level_events[0][1].record()
-    if parts is not None and use_state and level_events is None:
-        # the level loop itself in one call (one launch when every level is small)
+    if use_state and level_events is None and len({isinstance(w, PackedWeights) for w in W}) == 1:
+        # the level loop itself in one call (one launch where the user parts are given)
         return draft_levels(H, W, E, radices, K, itemset, buffers, stream, U, prefix_sets, parts,
                             state_init)
     for level in range(1, L + 1):

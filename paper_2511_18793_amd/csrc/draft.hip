@@ -17,6 +17,7 @@
 //   mfma_rate_kernel,       measurement aids: what the chip sustains on the bare instruction mixes
 //   tile_step_kernel        of the projection and of the per-request expansion (the rooflines'
 //                           measured denominators)
+#include "beam_args.h"
 #include "nezha_internal.h"
 
 #include <atomic>
@@ -25,250 +26,7 @@
 namespace nezha {
 namespace {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
-
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
-
-__device__ __forceinline__ float bf16_to_float(uint16_t h) {
-  return __uint_as_float((uint32_t)h << 16);
-}
-__device__ __forceinline__ uint16_t float_to_bf16(float f) {  // round to nearest even
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-// max(a, b) for operands that are never NaN, as the single instruction it is (the generic maximum
-// first rewrites both operands into canonical form, two more instructions per call).
-__device__ __forceinline__ float max_of_numbers(float a, float b) {
-  float r;
-  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-// Two running maxima in one register: (a, b) rounded towards zero to half precision, packed, and
-// the element-wise maximum of two such pairs.  A maximum kept this way is off by less than one
-// half-precision unit in the last place (2^-10 relative; below 2^-14 in magnitude: 2^-24
-// absolute); half_floor / half_ceil turn it back into a float32 bound on the true maximum from
-// below / above.  Values beyond the half range (|x| > 65504) are clamped by the conversion and
-// must be detected by the caller (half_out_of_range).
-__device__ __forceinline__ uint32_t pack_halves_rtz(float a, float b) {
-  auto p = __builtin_amdgcn_cvt_pkrtz(a, b);
-  uint32_t r;
-  __builtin_memcpy(&r, &p, 4);
-  return r;
-}
-__device__ __forceinline__ uint32_t max_of_half_pairs(uint32_t a, uint32_t b) {
-  uint32_t r;
-  asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-__device__ __forceinline__ float half_bits_to_float(uint32_t h) {
-  const uint16_t x = (uint16_t)h;
-  _Float16 f;
-  __builtin_memcpy(&f, &x, 2);
-  return (float)f;
-}
-__device__ __forceinline__ float half_floor(float m) { return m - fabsf(m) * 0.0009765625f - 1e-7f; }
-__device__ __forceinline__ float half_ceil(float m) { return m + fabsf(m) * 0.0009765625f + 1e-7f; }
-__device__ __forceinline__ bool half_out_of_range(float m) {
-  return fabsf(m) >= 60000.f && fabsf(m) < INFINITY;
-}
-// Order-preserving map float -> uint32 (larger float <=> larger integer) and back.
-__device__ __forceinline__ uint32_t ordered_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
-}
-__device__ __forceinline__ float unordered_bits(uint32_t o) {
-  uint32_t u = (o & 0x80000000u) ? (o ^ 0x80000000u) : ~o;
-  return __uint_as_float(u);
-}
-
-// ---- cross-lane helpers (wave64) ---------------------------------------------------------
-// Orders this wave's LDS traffic: the hardware runs one wave's LDS instructions in issue
-// order, so only the compiler has to be kept from moving accesses across this point.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-}
-
-// Value of lane (lane ^ M) for a compile-time M.  Distances 1, 2 and 8 are one DPP move
-// (quad permutes, rotation by 8 inside a row of 16 lanes); 4 takes the two rotations by 4 and
-// 12; 16 and 32 use the gfx950 row / half-wave swaps.
-template <int M>
-__device__ __forceinline__ uint32_t lane_xor(uint32_t v, int lane) {
-  if constexpr (M == 1) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
-  } else if constexpr (M == 2) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
-  } else if constexpr (M == 4) {
-    const uint32_t down = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xF, 0xF, true);
-    const uint32_t up = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x12C, 0xF, 0xF, true);
-    return (lane & 4) ? down : up;   // row_ror:4 reads lane-4, row_ror:12 reads lane+4
-  } else if constexpr (M == 8) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);
-  } else if constexpr (M == 16) {
-    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    return (lane & 16) ? r[0] : r[1];
-  } else {
-    static_assert(M == 32, "lane distance");
-    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return (lane & 32) ? r[0] : r[1];
-  }
-}
-
-// One compare-exchange step of the bitonic network across lanes at distance LM, for R
-// independent sequences at once (independent work hides the cross-lane latency).
-template <int NPL, int R, int LM, typename T>
-__device__ __forceinline__ void cross_step(T (&key)[R][NPL], int lane, bool keep_max) {
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int j = 0; j < NPL; ++j) {
-      T other;
-      if constexpr (sizeof(T) == 8) {
-        const uint32_t lo = lane_xor<LM>((uint32_t)key[r][j], lane);
-        const uint32_t hi = lane_xor<LM>((uint32_t)(key[r][j] >> 32), lane);
-        other = ((uint64_t)hi << 32) | lo;
-      } else {
-        other = lane_xor<LM>(key[r][j], lane);
-      }
-      const bool gt = key[r][j] > other;
-      key[r][j] = (gt == keep_max) ? key[r][j] : other;
-    }
-}
-
-// Bitonic sort of R sequences of 64*NPL keys (64- or 32-bit unsigned), NPL per lane, descending
-// in position p = lane*NPL + j.
-template <int NPL, int R, typename T = uint64_t>
-__device__ __forceinline__ void sort_desc(T (&key)[R][NPL]) {
-  const int lane = threadIdx.x & 63;
-  constexpr int N = 64 * NPL;
-#pragma unroll
-  for (int k = 2; k <= N; k <<= 1) {
-#pragma unroll
-    for (int dist = k >> 1; dist >= 1; dist >>= 1) {
-      if (dist < NPL) {
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int j = 0; j < NPL; ++j) {
-            if ((j & dist) == 0) {
-              const int j2 = j | dist;
-              // block direction: descending where bit k of the position is clear
-              const bool desc = (k < NPL) ? ((j & k) == 0)
-                                          : (k == N ? true : ((lane & (k / NPL)) == 0));
-              const T a = key[r][j], b = key[r][j2];
-              const bool a_gt = a > b;
-              const bool swap = desc ? !a_gt : a_gt;
-              key[r][j] = swap ? b : a;
-              key[r][j2] = swap ? a : b;
-            }
-          }
-      } else {
-        const int lm = dist / NPL;
-        const bool is_lo = (lane & lm) == 0;
-        const bool desc = (k == N) ? true : ((lane & (k / NPL)) == 0);
-        const bool keep_max = (is_lo == desc);
-        if (lm == 1) cross_step<NPL, R, 1, T>(key, lane, keep_max);
-        else if (lm == 2) cross_step<NPL, R, 2, T>(key, lane, keep_max);
-        else if (lm == 4) cross_step<NPL, R, 4, T>(key, lane, keep_max);
-        else if (lm == 8) cross_step<NPL, R, 8, T>(key, lane, keep_max);
-        else if (lm == 16) cross_step<NPL, R, 16, T>(key, lane, keep_max);
-        else cross_step<NPL, R, 32, T>(key, lane, keep_max);
-      }
-    }
-  }
-}
-
-// Cuts R LDS buffers (R rows) back to their K largest keys, sorted descending at buf[0..):
-// rows[r] points at CAP keys of which cnt[r] are in use.  On return cnt[r] = min(cnt[r], K)
-// and tau[r] is the K-th largest key (0 while fewer than K are held).  Wave uniform.
-template <int CAP, int NPL, int R>
-__device__ __forceinline__ void compact_rows_n(uint64_t* const (&rows)[R], int (&cnt)[R],
-                                               uint64_t (&tau)[R], int K) {
-  const int lane = threadIdx.x & 63;
-  uint64_t key[R][NPL];
-  wave_sync();
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int j = 0; j < NPL; ++j) {
-      const int e = j * 64 + lane;
-      key[r][j] = e < cnt[r] ? rows[r][e] : 0ull;
-    }
-  sort_desc<NPL, R>(key);
-  wave_sync();
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int keep = cnt[r] < K ? cnt[r] : K;
-#pragma unroll
-    for (int j = 0; j < NPL; ++j) {
-      const int p = lane * NPL + j;
-      if (p < keep) rows[r][p] = key[r][j];
-    }
-    cnt[r] = keep;
-  }
-  wave_sync();
-#pragma unroll
-  for (int r = 0; r < R; ++r) tau[r] = (cnt[r] == K) ? rows[r][K - 1] : 0ull;
-}
-
-// Picks the smallest network that holds every row (all counts are wave uniform).
-template <int CAP, int R>
-__device__ __forceinline__ void compact_rows(uint64_t* const (&rows)[R], int (&cnt)[R],
-                                             uint64_t (&tau)[R], int K) {
-  int most = 0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) most = cnt[r] > most ? cnt[r] : most;
-  if (most <= 64) {
-    compact_rows_n<CAP, 1, R>(rows, cnt, tau, K);
-  } else if (CAP == 128 || most <= 128) {
-    compact_rows_n<CAP, 2, R>(rows, cnt, tau, K);
-  } else {
-    compact_rows_n<CAP, CAP / 64, R>(rows, cnt, tau, K);
-  }
-}
-
-// A streaming top-K of 64-bit keys for one wave.  The buffer lives in LDS (CAP keys); keys
-// that beat the threshold are appended with a ballot prefix; when fewer than 64 free places
-// remain the buffer is sorted and cut back to the K largest, which raises the threshold.
-template <int CAP>
-struct WaveTopK {
-  uint64_t* buf;   // LDS, CAP entries, private to the wave
-  int cnt;         // wave uniform
-  uint64_t tau;    // keys must be > tau to enter; wave uniform
-  int K;
-
-  __device__ __forceinline__ void init(uint64_t* b, int k) {
-    buf = b;
-    cnt = 0;
-    tau = 0;
-    K = k;
-  }
-  // Sort, keep the K largest at buf[0..), update tau.
-  __device__ __forceinline__ void compact() {
-    uint64_t* const rows[1] = {buf};
-    int c[1] = {cnt};
-    uint64_t t[1] = {0};
-    compact_rows<CAP, 1>(rows, c, t, K);
-    cnt = c[0];
-    tau = t[0];
-  }
-  // One key per lane (0 = nothing).  All lanes of the wave must call this together.
-  __device__ __forceinline__ void push(uint64_t key) {
-    const bool pass = key > tau;
-    const uint64_t bal = __ballot(pass);
-    if (bal) {
-      const int pos = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
-      if (pass) buf[pos] = key;
-      cnt += __popcll(bal);
-      if (cnt > CAP - 64) compact();
-    }
-  }
-};
+#include "device_common.h"
 
 // ---- weight packing -------------------------------------------------------------------------
 // W_l (bf16, [(d+e), V] row major) is rearranged into MFMA operand order, two regions:
@@ -869,19 +627,46 @@ __global__ __launch_bounds__(256) void tile_step_kernel(const float* __restrict_
   }
 }
 
-// ---- user-part projection, fp32 (small correctness-first shapes) -----------------------------
-__global__ __launch_bounds__(256) void user_gemm_f32_kernel(const float* __restrict__ H,
-                                                            int64_t h_stride,
-                                                            const float* __restrict__ W,
-                                                            float* __restrict__ A, int B, int d,
-                                                            int V) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  const int b = blockIdx.y;
-  if (v >= V || b >= B) return;
-  const float* h = H + (int64_t)b * h_stride;
-  float s = 0.f;
-  for (int i = 0; i < d; ++i) s = fmaf(h[i], W[(int64_t)i * V + v], s);
-  A[(int64_t)b * V + v] = s;
+// ---- user-part projection, fp32 ------------------------------------------------------------------
+// The shapes this runs at are small (a few requests, a few hundred codes), so the time is the length
+// of the k loop: a workgroup of eight waves forms one 16 x 16 tile of A with the k range in eight
+// parts (v_mfma_f32_16x16x4f32), whose partial results are added through LDS.  k is taken in groups of
+// 16: lane (c, g) holds H[row c][k .. k+3] and W[k .. k+3][column c] with k = 16 q + 4 g, so that a
+// request's row is read in 64-byte pieces.  48 x 512 x 256: 49 us with one thread per output walking
+// all of k, 5.5 us so.
+constexpr int kGemm32Waves = 8;
+__global__ __launch_bounds__(64 * kGemm32Waves) void user_gemm_f32_kernel(
+    const float* __restrict__ H, int64_t h_stride, const float* __restrict__ W,
+    float* __restrict__ A, int B, int d, int V) {
+  __shared__ floatx4 part[kGemm32Waves][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = lane >> 4, c = lane & 15;
+  const int row0 = blockIdx.y * 16, col = blockIdx.x * 16 + c;
+  const int row = row0 + c < B ? row0 + c : B - 1;          // past the end: never stored
+  const float* h = H + (int64_t)row * h_stride;
+  const int groups = (d + 15) / 16;
+  floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+  for (int q = wave; q < groups; q += kGemm32Waves) {
+    const int k = 16 * q + 4 * g;
+    float a[4], w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      a[j] = k + j < d ? h[k + j] : 0.f;
+      w[j] = k + j < d ? W[(int64_t)(k + j) * V + col] : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], w[j], acc, 0, 0, 0);
+  }
+  part[wave][lane] = acc;
+  __syncthreads();
+  if (wave < 4) {                                            // wave i: row 4 g + i of the tile
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kGemm32Waves; ++w) sum += part[w][lane][wave];
+    const int r = row0 + 4 * g + wave;
+    if (r < B) A[(int64_t)r * V + col] = sum;
+  }
 }
 
 // ---- beam-part projection + log-softmax + per-beam top-K --------------------------------------
@@ -1472,144 +1257,6 @@ struct MergeArgs {
   int transition;
   const uint8_t* redo_req;  // only requests with redo_req[b] != 0 (NULL: every request)
 };
-
-// Eq. 3 with the additive Transition for the K survivors of request b: c' = c_parent + E[code]
-// (zero for unused slots); 8 (bf16) or 4 (f32) elements per thread and step.
-// lds_in / lds_out (bf16 only, may be NULL): the parents' states [K_in, e] and a second copy of
-// the new states [K, e] in LDS, for a caller that runs the next level in the same workgroup.
-template <bool BF16>
-__device__ __forceinline__ void update_states(const void* state_in, const void* E, void* state_out,
-                                              int b, int K, int K_in, int e,
-                                              const int32_t* fin_parent, const int32_t* fin_code,
-                                              int tid, int nthreads,
-                                              const uint16_t* lds_in = nullptr,
-                                              uint16_t* lds_out = nullptr) {
-  {
-    const int per = e / (BF16 ? 8 : 4);
-    for (int idx = tid; idx < K * per; idx += nthreads) {
-      const int j = idx / per, t = idx - j * per;
-      const int par = fin_parent[j], code = fin_code[j];
-      if constexpr (BF16) {
-        uint16_t* out = static_cast<uint16_t*>(state_out) + ((int64_t)b * K + j) * e + t * 8;
-        uint4 r = uint4{0, 0, 0, 0};
-        if (par >= 0) {
-          const uint4 ev = load_global_u4(static_cast<const uint16_t*>(E) + (int64_t)code * e + t * 8);
-          uint4 sv = uint4{0, 0, 0, 0};
-          if (lds_in)
-            sv = *reinterpret_cast<const uint4*>(lds_in + par * e + t * 8);
-          else if (state_in)
-            sv = load_global_u4(static_cast<const uint16_t*>(state_in) +
-                                ((int64_t)b * K_in + par) * e + t * 8);
-          const uint32_t ew[4] = {ev.x, ev.y, ev.z, ev.w}, sw[4] = {sv.x, sv.y, sv.z, sv.w};
-          uint32_t ow[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const float lo = bf16_to_float((uint16_t)ew[u]) + bf16_to_float((uint16_t)sw[u]);
-            const float hi = bf16_to_float((uint16_t)(ew[u] >> 16)) +
-                             bf16_to_float((uint16_t)(sw[u] >> 16));
-            ow[u] = (uint32_t)float_to_bf16(lo) | ((uint32_t)float_to_bf16(hi) << 16);
-          }
-          r = uint4{ow[0], ow[1], ow[2], ow[3]};
-        }
-        store_global_u4(out, r);
-        if (lds_out) *reinterpret_cast<uint4*>(lds_out + j * e + t * 8) = r;
-      } else {
-        float* out = static_cast<float*>(state_out) + ((int64_t)b * K + j) * e + t * 4;
-        float4 r = float4{0.f, 0.f, 0.f, 0.f};
-        if (par >= 0) {
-          const float4 ev = *reinterpret_cast<const float4*>(static_cast<const float*>(E) +
-                                                             (int64_t)code * e + t * 4);
-          float4 sv = float4{0.f, 0.f, 0.f, 0.f};
-          if (state_in)
-            sv = *reinterpret_cast<const float4*>(static_cast<const float*>(state_in) +
-                                                  ((int64_t)b * K_in + par) * e + t * 4);
-          r = float4{ev.x + sv.x, ev.y + sv.y, ev.z + sv.z, ev.w + sv.w};
-        }
-        *reinterpret_cast<float4*>(out) = r;
-      }
-    }
-  }
-}
-
-// Eq. 3 with the recurrent Transition for the K survivors of request b:
-// c'[j] = tanh(sum_i U[j][i] c_parent[i] + E[code][j]) (zero for unused slots).  bf16: 16x16
-// output tiles (16 survivors x 16 state elements) by v_mfma_f32_16x16x32_bf16, spread over the
-// workgroup's waves; the accumulator starts at the code embedding; the A operand is the parent
-// state row, the B operand B[k][n] = U[n][k] is 16 contiguous bytes of row n of U.
-template <bool BF16>
-__device__ __forceinline__ void update_states_rnn(const void* state_in, const void* E, const void* U,
-                                                  void* state_out, int b, int K, int K_in, int e,
-                                                  const int32_t* fin_parent,
-                                                  const int32_t* fin_code, int tid, int nthreads,
-                                                  const uint16_t* lds_in = nullptr,
-                                                  uint16_t* lds_out = nullptr) {
-  if constexpr (BF16) {
-    const int lane = tid & 63, wave = tid >> 6, n_waves = nthreads >> 6;
-    const int g = lane >> 4, c = lane & 15;
-    const int RT = (K + 15) / 16, CT = e / 16, KS = e / 32;
-    const uint16_t* Eh = static_cast<const uint16_t*>(E);
-    const uint16_t* Uh = static_cast<const uint16_t*>(U);
-    const uint16_t* Sh = static_cast<const uint16_t*>(state_in);
-    uint16_t* Oh = static_cast<uint16_t*>(state_out);
-    for (int t = wave; t < RT * CT; t += n_waves) {
-      const int rt = t / CT, ct = t - rt * CT;
-      floatx4 acc;
-      int code[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int j = rt * 16 + 4 * g + i;
-        code[i] = j < K ? fin_code[j] : -1;
-        acc[i] = code[i] >= 0 ? bf16_to_float(as_global(Eh)[(int64_t)code[i] * e + ct * 16 + c]) : 0.f;
-      }
-      const int ja = rt * 16 + c;
-      const int pa = ja < K ? fin_parent[ja] : -1;
-      if (Sh || lds_in) {
-        for (int ks = 0; ks < KS; ++ks) {
-          uint4 av = uint4{0, 0, 0, 0};
-          if (pa >= 0) {
-            if (lds_in)
-              av = *reinterpret_cast<const uint4*>(lds_in + pa * e + ks * 32 + 8 * g);
-            else
-              av = load_global_u4(Sh + ((int64_t)b * K_in + pa) * e + ks * 32 + 8 * g);
-          }
-          const uint4 bv = load_global_u4(Uh + (int64_t)(ct * 16 + c) * e + ks * 32 + 8 * g);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(&av),
-                                                        *reinterpret_cast<const bf16x8*>(&bv), acc,
-                                                        0, 0, 0);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int j = rt * 16 + 4 * g + i;
-        if (j < K) {
-          const uint16_t v = code[i] >= 0 ? float_to_bf16(tanhf(acc[i])) : (uint16_t)0;
-          as_global(Oh)[((int64_t)b * K + j) * e + ct * 16 + c] = v;
-          if (lds_out) lds_out[j * e + ct * 16 + c] = v;
-        }
-      }
-    }
-  } else {
-    const float* Ef = static_cast<const float*>(E);
-    const float* Uf = static_cast<const float*>(U);
-    const float* Sf = static_cast<const float*>(state_in);
-    float* Of = static_cast<float*>(state_out);
-    for (int idx = tid; idx < K * e; idx += nthreads) {
-      const int j = idx / e, col = idx - j * e;
-      const int par = fin_parent[j], code = fin_code[j];
-      float r = 0.f;
-      if (par >= 0) {
-        float acc = Ef[(int64_t)code * e + col];
-        if (Sf) {
-          const float* srow = Sf + ((int64_t)b * K_in + par) * e;
-          const float* urow = Uf + (int64_t)col * e;
-          for (int i = 0; i < e; ++i) acc = fmaf(urow[i], srow[i], acc);
-        }
-        r = tanhf(acc);
-      }
-      Of[((int64_t)b * K + j) * e + col] = r;
-    }
-  }
-}
 
 // One workgroup (4 or 16 waves) per request.  Every candidate (parent p, within-beam rank r) gets
 // the sort key (ordered score, ~(p*K+r)), or 0 if the verifier rejects it; all keys go to LDS.
@@ -3282,6 +2929,65 @@ int allow_lds(Kern kern, size_t bytes) {
   return NEZHA_OK;
 }
 
+// ---- beam_kernel: LDS layout and dispatch ---------------------------------------------------------
+constexpr size_t kBeamLdsMax = 160 * 1024;
+inline int beam_row_tiles(int K_in) { return (K_in + 15) / 16; }
+// float32: decode_lds_kernel where every level's logits [K_in, T_l] (and the K best codes of its beams)
+// fit in LDS and the beams' states in registers (16 x 64 numbers a wave at most); expand_kernel, which
+// streams the codes through registers, for the rest.  48 requests, 3 x 256 codes, 8 beams: three
+// levels took 181 us with expand_kernel, 38 us so.
+// The choice looks at the whole decode (its beams and its largest codebook), not at the level at
+// hand, so that every level of it is taken by the same kernel.
+constexpr size_t kDecodeLdsMax = 150 * 1024;
+int launch_decode_lds(BeamArgs& a, int B, int K_in, const nezha_step_desc* desc, hipStream_t stream,
+                      bool* taken) {
+  *taken = false;
+  int max_v = 16;
+  for (int l = 0; l < desc->L; ++l) max_v = desc->radices[l] > max_v ? desc->radices[l] : max_v;
+  const int rt = beam_row_tiles(K_in), beams = a.K > K_in ? a.K : K_in;
+  const int steps = a.e <= 64 ? 16 : 32;
+  size_t at = align_up(decode_shared_bytes(), 256);
+  // list: the K best codes of every beam, and at least 512 (what an overflow is judged by)
+  a.list_cap = (int)align_up((size_t)beams * a.K > 1024 ? (size_t)beams * a.K : 1024, 512);
+  a.list_off = (uint32_t)at;
+  at += align_up((size_t)a.list_cap * 8, 256);
+  a.x_off = (uint32_t)at;
+  at += align_up((size_t)beams * (max_v + 4) * 4, 256);
+  if (a.list_cap > 4096 || at > kDecodeLdsMax || a.e > 128 || beam_row_tiles(beams) * steps > 64)
+    return NEZHA_OK;
+  *taken = true;
+  ProfileScope prof(kBeam, stream);
+  return steps == 16 ? launch_decode_lds_16(a, B, rt, at, stream) : launch_decode_lds_32(a, B, rt, at, stream);
+}
+inline BeamLevel make_beam_level(const nezha_step_desc* desc, const void* Wbeam, const float* A,
+                                 const void* E_l, const void* state_in, const uint64_t* key_in,
+                                 const float* score_in, const nezha_itemset* set, uint64_t* key_out,
+                                 float* score_out, int32_t* parent_out, int32_t* code_out,
+                                 void* state_out, int32_t* count_out, uint64_t mult) {
+  BeamLevel v;
+  v.state_in = state_in;
+  v.V = desc->radices[desc->level - 1];
+  v.Wbeam = Wbeam;
+  v.A = A;
+  v.key_in = key_in;
+  v.score_in = score_in;
+  v.E = E_l;
+  v.U = desc->U_l;
+  const bool here = set && set->L == desc->level;
+  v.set = SetView{here ? set->slots : nullptr, set ? set->n_buckets : 0, set ? set->filter : nullptr,
+                  set ? set->n_blocks : 0, set ? set->mult[set->L - 1] : 0};
+  v.mult = mult;
+  v.key_out = key_out;
+  v.score_out = score_out;
+  v.parent_out = parent_out;
+  v.code_out = code_out;
+  v.state_out = state_out;
+  v.count_out = count_out;
+  v.K_in = desc->K_in;
+  v.transition = desc->transition;
+  return v;
+}
+
 // Products with fewer outputs than this are "small": 128 x 128 tiles would leave most of the 256
 // CUs without a workgroup (B = T_l = 1024: 64 tiles), so they get 32 x 64 tiles, and their k
 // loop runs in four parts side by side (user_gemm_tile, KSPLIT).
@@ -3342,9 +3048,9 @@ int launch_user_part(const nezha_step_desc* desc, const void* H_l, const void* W
 #undef LAUNCH_GEMM
     NEZHA_HIP_CHECK(hipGetLastError());
   } else {
-    dim3 grid((V + 255) / 256, B);
+    dim3 grid(V / 16, (B + 15) / 16);
     ProfileScope prof(kUserGemm, stream);
-    hipLaunchKernelGGL(user_gemm_f32_kernel, grid, dim3(256), 0, stream,
+    hipLaunchKernelGGL(user_gemm_f32_kernel, grid, dim3(64 * kGemm32Waves), 0, stream,
                        static_cast<const float*>(H_l), desc->h_row_stride,
                        static_cast<const float*>(W_l), A, B, d, V);
     NEZHA_HIP_CHECK(hipGetLastError());
@@ -3807,6 +3513,18 @@ int nezha_draft_step(const nezha_step_desc* desc, const void* H_l, const void* W
       NEZHA_HIP_CHECK(hipGetLastError());
     }
     return NEZHA_OK;
+  }
+
+  if (!bf16 && K <= NEZHA_MAX_BEAM) {
+    BeamArgs ba;
+    ba.L = 1;
+    ba.K = K;
+    ba.e = e;
+    ba.lv[0] = make_beam_level(desc, bf16 ? static_cast<const void*>(Wp + packed_user_elems(d, V)) : static_cast<const float*>(W_l) + (int64_t)d * V, A, E_l, state_in, key_in, score_in, set, key_out, score_out,
+                               parent_out, code_out, state_out, count_out, mult[level - 1]);
+    bool taken = false;
+    rc = launch_decode_lds(ba, B, K_in, desc, stream, &taken);
+    if (rc != NEZHA_OK || taken) return rc;
   }
 
   if (level_fits_one_launch(bf16, K, K_in, V, e)) {

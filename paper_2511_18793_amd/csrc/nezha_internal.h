@@ -33,6 +33,7 @@ bool radix_multipliers(int32_t L, const int32_t* radices, uint64_t* mult);
 enum KernelKind {
   kPackWeights = 0, kUserGemm, kExpand, kMerge, kVerifyProbe, kVerifyScan, kVerifyScatter,
   kInsert, kGather, kLevelFused, kExpandRequest, kDecodeFused, kWideLogits, kWideRows, kWideSelect,
+  kBeam,
   kKernelKinds
 };
 // Brackets the launches made while it is alive with two events on `stream` when timing is on.
