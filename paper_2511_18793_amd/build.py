@@ -8,7 +8,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 # (source, object name, extra flags); the slowest first
-UNITS = [("beam.hip", "beam_%d" % k, ["-DBEAM_KST=%d" % k]) for k in (32, 16)]
+UNITS = [("beam.hip", "beam_%d" % k, ["-DBEAM_KST=%d" % k]) for k in (8, 4, 3, 2, 1, 32, 16)]
 UNITS += [("draft.hip", "draft", []), ("itemset.hip", "itemset", [])]
 OUT = os.path.join(HERE, "libnezha.so")
 

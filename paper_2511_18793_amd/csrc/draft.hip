@@ -2932,6 +2932,22 @@ int allow_lds(Kern kern, size_t bytes) {
 // ---- beam_kernel: LDS layout and dispatch ---------------------------------------------------------
 constexpr size_t kBeamLdsMax = 160 * 1024;
 inline int beam_row_tiles(int K_in) { return (K_in + 15) / 16; }
+// Every level of the decode is one for level_small_kernel / decode_small_kernel.
+inline bool decode_is_small(const nezha_step_desc* desc) {
+  for (int l = 0; l < desc->L; ++l)
+    if (!level_fits_one_launch(desc->dtype == NEZHA_BF16, desc->K, 1, desc->radices[l], desc->e)) return false;
+  return true;
+}
+// Which levels beam_kernel takes: bf16, beams of up to 128 (codes take 24 bits of a list entry), unless
+// the decode is small: with up to 32 beams and 512 codes decode_small_kernel keeps a level's logits in
+// registers and its time hardly depends on how many candidates are items, while one request in many
+// that has to look at all of its candidates sets beam_kernel's (256 requests, 3 x 256 codes, 20 beams:
+// 30 us against 60 to 90 us).
+inline bool beam_takes(const nezha_step_desc* desc, int K_in, int V) {
+  const int K = desc->K;
+  return K <= NEZHA_MAX_BEAM && K_in <= NEZHA_MAX_BEAM && V <= (1 << 20) &&
+         !(decode_is_small(desc) && K_in <= kLevelRows);
+}
 // float32: decode_lds_kernel where every level's logits [K_in, T_l] (and the K best codes of its beams)
 // fit in LDS and the beams' states in registers (16 x 64 numbers a wave at most); expand_kernel, which
 // streams the codes through registers, for the rest.  48 requests, 3 x 256 codes, 8 beams: three
@@ -2958,6 +2974,49 @@ int launch_decode_lds(BeamArgs& a, int B, int K_in, const nezha_step_desc* desc,
   *taken = true;
   ProfileScope prof(kBeam, stream);
   return steps == 16 ? launch_decode_lds_16(a, B, rt, at, stream) : launch_decode_lds_32(a, B, rt, at, stream);
+}
+// Fills in the layout for levels whose K_in is at most K_in and launches.
+int launch_beam(BeamArgs& a, int B, int K_in, hipStream_t stream) {
+  const int rt = beam_row_tiles(K_in);
+  bool verify = false, any_set = false;
+  size_t mask = 0;
+  for (int l = 0; l < a.L; ++l) {
+    const BeamLevel& v = a.lv[l];
+    any_set = any_set || v.set.slots != nullptr;
+    if (v.K_in == 1 && l == 0 && !v.state_in) continue;    // level 1: no matrix, no region x
+    if (v.set.slots) {
+      verify = true;
+      const size_t m = (size_t)(v.V / 16) * rt * 32;
+      mask = m > mask ? m : mask;
+    }
+  }
+  size_t at = align_up(beam_shared_bytes(), 256);
+  a.list_cap = kBeamList;
+  a.list_off = (uint32_t)at;
+  at += align_up((size_t)(kBeamList + NEZHA_MAX_BEAM) * 8, 256);
+  a.x_off = (uint32_t)at;
+  a.mask_in_lds = 0;
+  if (verify) {
+    size_t x = (size_t)16 * rt * (8 * 16 + 1) * 4;
+    if (mask > x && at + mask <= kBeamLdsMax) x = mask;
+    a.mask_in_lds = mask <= x;
+    at += align_up(x, 256);
+  }
+  a.status_off = (uint32_t)at;
+  if (any_set) at += kBeamStatusBytes;
+  a.state_off = (uint32_t)at;
+  a.state_bufs = 0;
+  if (a.L > 1) {
+    const size_t one = align_up((size_t)a.K * (a.e + 8) * 2, 256);
+    a.state_bufs = at + 2 * one <= kBeamLdsMax ? 2 : at + one <= kBeamLdsMax ? 1 : 0;
+    at += one * a.state_bufs;
+  }
+  ProfileScope prof(kBeam, stream);
+  if (a.e <= 32) return launch_beam_1(a, B, rt, at, stream);
+  if (a.e <= 64) return launch_beam_2(a, B, rt, at, stream);
+  if (a.e <= 96) return launch_beam_3(a, B, rt, at, stream);
+  if (a.e <= 128) return launch_beam_4(a, B, rt, at, stream);
+  return launch_beam_8(a, B, rt, at, stream);
 }
 inline BeamLevel make_beam_level(const nezha_step_desc* desc, const void* Wbeam, const float* A,
                                  const void* E_l, const void* state_in, const uint64_t* key_in,
@@ -3515,13 +3574,14 @@ int nezha_draft_step(const nezha_step_desc* desc, const void* H_l, const void* W
     return NEZHA_OK;
   }
 
-  if (!bf16 && K <= NEZHA_MAX_BEAM) {
+  if (beam_takes(desc, K_in, V)) {
     BeamArgs ba;
     ba.L = 1;
     ba.K = K;
     ba.e = e;
     ba.lv[0] = make_beam_level(desc, bf16 ? static_cast<const void*>(Wp + packed_user_elems(d, V)) : static_cast<const float*>(W_l) + (int64_t)d * V, A, E_l, state_in, key_in, score_in, set, key_out, score_out,
                                parent_out, code_out, state_out, count_out, mult[level - 1]);
+    if (bf16) return launch_beam(ba, B, K_in, stream);
     bool taken = false;
     rc = launch_decode_lds(ba, B, K_in, desc, stream, &taken);
     if (rc != NEZHA_OK || taken) return rc;
@@ -3846,6 +3906,37 @@ static int draft_levels_checked(const nezha_step_desc* desc, const nezha_level_i
   const int L = desc->L;
   const bool bf16 = desc->dtype == NEZHA_BF16;
   const int K = desc->K;
+  // one launch for all levels where beam_kernel takes each of them and has its user part
+  bool beam = desc->w_packed == 1 && desc->B > 0;
+  for (int l = 1; l <= L && beam; ++l)
+    beam = bf16 && beam_takes(desc, l == 1 ? 1 : K, desc->radices[l - 1]) && io[l - 1].user_part != nullptr;
+  if (beam) {
+    uint64_t mult[NEZHA_MAX_LEVELS];
+    if (!radix_multipliers(L, desc->radices, mult))
+      return fail(NEZHA_ERANGE, "radices must be >= 1 with a product of at most 2^64-1");
+    BeamArgs ba;
+    ba.L = L;
+    ba.K = K;
+    ba.e = desc->e;
+    nezha_step_desc dl = *desc;
+    const void* state = desc->state_init;
+    const uint64_t* key = nullptr;
+    const float* score = nullptr;
+    for (int l = 1; l <= L; ++l) {
+      const nezha_level_io& x = io[l - 1];
+      dl.level = l;
+      dl.K_in = l == 1 ? 1 : K;
+      dl.U_l = x.U_l;
+      ba.lv[l - 1] = make_beam_level(&dl, static_cast<const uint16_t*>(x.W_l) + packed_user_elems(desc->d, desc->radices[l - 1]), x.user_part, x.E_l, state,
+                                     key, score, x.set, x.key_out, x.score_out, x.parent_out,
+                                     x.code_out, x.state_out, x.count_out, mult[l - 1]);
+      state = x.state_out;
+      key = x.key_out;
+      score = x.score_out;
+    }
+    for (int l = L; l < NEZHA_MAX_LEVELS; ++l) ba.lv[l] = ba.lv[L - 1];
+    return launch_beam(ba, desc->B, L > 1 ? K : 1, (hipStream_t)hip_stream);
+  }
   // one launch for all levels when every level fits the single-launch kernel and has its user part
   bool one_launch = bf16 && desc->w_packed == 1 && desc->B > 0;
   int max_v = 0;

@@ -11,6 +11,13 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("B,d,e,V,K,L,dtype", [
+    (5, 64, 128, 528, 16, 3, "bf16"),     # one row tile, the first codebook past the small kernel's
+    (3, 64, 32, 16, 16, 4, "bf16"),       # one column tile for eight waves
+    (4, 64, 64, 144, 33, 3, "bf16"),      # a third row tile with one beam
+    (3, 96, 96, 1040, 48, 3, "bf16"),     # three full row tiles, 65 column tiles
+    (2, 64, 160, 256, 49, 2, "bf16"),     # a state between two instance widths
+    (2, 64, 256, 320, 128, 3, "bf16"),    # eight row tiles, operands read from LDS
+    (300, 32, 32, 544, 4, 3, "bf16"),     # more requests than compute units
     (7, 33, 32, 80, 9, 3, "f32"),
     (17, 65, 128, 256, 16, 3, "f32"),     # rows of A past the last full tile
     (2, 20, 256, 48, 33, 2, "f32"),
