@@ -94,7 +94,8 @@ def _ptr(t):
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the handle of torch.cuda.current_stream() without building the Stream object
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return C.c_void_p(stream.cuda_stream)
 
 
@@ -180,9 +181,12 @@ def verify_tuples(itemset, codes, out_mask=None, out_index=None, out_count=None,
         out_count = torch.empty(1, dtype=torch.int64, device=dev)
     if workspace is None:
         workspace = torch.empty(max(16, verify_workspace(n)), dtype=torch.uint8, device=dev)
-    _check(load_library().nezha_verify_tuples(itemset._h, _ptr(codes), n, _ptr(out_mask),
-                                              _ptr(out_index), _ptr(out_count), _ptr(workspace),
-                                              workspace.numel(), _stream(stream)))
+    # (plain integers: the declared argument types convert them; a small batch is over in a few us)
+    _check((_LIB or load_library()).nezha_verify_tuples(
+        itemset._h, codes.data_ptr(), n, out_mask.data_ptr(),
+        None if out_index is None else out_index.data_ptr(),
+        None if out_count is None else out_count.data_ptr(), workspace.data_ptr(),
+        workspace.numel(), _stream(stream)))
     return out_mask, out_index, out_count
 
 

@@ -209,6 +209,19 @@ __global__ void filter_kernel(const uint64_t* __restrict__ slots, uint64_t n_slo
 constexpr int kVerifyThreads = 256;
 constexpr int kPerThread = 4;                                 // consecutive tuples per lane
 constexpr int kVerifyBlock = kVerifyThreads * kPerThread;     // tuples per workgroup
+// Batches that do not fill the chip's lanes (256 CUs x 2048) with four tuples each take one tuple per
+// lane: the call then lasts one chain of dependent reads (codes, bucket), not four.  Their block
+// counts (<= 256) are 16-bit numbers in the room of the larger blocks' 32-bit ones.  5120 tuples:
+// the call takes 11.0 us with four tuples per lane and 8.8 with one (and a shorter way through the host).
+constexpr int64_t kVerifyOnePerLane = (int64_t)256 * 2048;
+template <int PER>
+struct VerifyCount {
+  typedef int32_t type;
+};
+template <>
+struct VerifyCount<1> {
+  typedef uint16_t type;
+};
 constexpr int64_t kFusedPrefixBlocks = 16384;                 // above this a scan kernel runs
 
 // Pass 1: pack + probe, write the mask bytes and the number of accepted tuples per block.
@@ -217,16 +230,16 @@ constexpr int64_t kFusedPrefixBlocks = 16384;                 // above this a sc
 // from.  (Measured against this on the stress workload, 78 us per call: all of a lane's home
 // buckets requested at once, 4 / 8 / 16 per lane: 138 / 156 / 195 us; eight lanes per bucket with
 // the keys staged through LDS: 90 us.)
-template <int L>
+template <int L, int PER>
 __global__ __launch_bounds__(kVerifyThreads) void verify_probe_kernel(
     const int32_t* __restrict__ codes, int64_t n, Radix r, SetView set,
-    uint8_t* __restrict__ mask, int32_t* __restrict__ block_count) {
+    uint8_t* __restrict__ mask, typename VerifyCount<PER>::type* __restrict__ block_count) {
   __shared__ int32_t wave_count[kVerifyThreads / 64];
-  const int64_t base = ((int64_t)blockIdx.x * kVerifyThreads + threadIdx.x) * kPerThread;
-  uint64_t key[kPerThread];
-  bool ok[kPerThread];
+  const int64_t base = ((int64_t)blockIdx.x * kVerifyThreads + threadIdx.x) * PER;
+  uint64_t key[PER];
+  bool ok[PER];
 #pragma unroll
-  for (int j = 0; j < kPerThread; ++j) {
+  for (int j = 0; j < PER; ++j) {
     ok[j] = false;
     key[j] = 0;
     if (base + j < n) {
@@ -241,16 +254,16 @@ __global__ __launch_bounds__(kVerifyThreads) void verify_probe_kernel(
   int cnt = 0;
   uint32_t bits = 0;
 #pragma unroll
-  for (int j = 0; j < kPerThread; ++j) {
+  for (int j = 0; j < PER; ++j) {
     bool in = ok[j] && set_probe(set, key[j]);
     bits |= (in ? 1u : 0u) << (8 * j);
     cnt += in ? 1 : 0;
   }
-  if (base + kPerThread <= n && (reinterpret_cast<uintptr_t>(mask) & 3) == 0) {
+  if (PER == 4 && base + PER <= n && (reinterpret_cast<uintptr_t>(mask) & 3) == 0) {
     *reinterpret_cast<uint32_t*>(mask + base) = bits;
   } else {
 #pragma unroll
-    for (int j = 0; j < kPerThread; ++j)
+    for (int j = 0; j < PER; ++j)
       if (base + j < n) mask[base + j] = (bits >> (8 * j)) & 1u;
   }
   // block total: wave reduction by cross-lane adds, then a 4-entry LDS sum
@@ -260,7 +273,7 @@ __global__ __launch_bounds__(kVerifyThreads) void verify_probe_kernel(
   if (threadIdx.x == 0) {
     int s = 0;
     for (int w = 0; w < kVerifyThreads / 64; ++w) s += wave_count[w];
-    block_count[blockIdx.x] = s;
+    block_count[blockIdx.x] = (typename VerifyCount<PER>::type)s;
   }
 }
 
@@ -300,9 +313,10 @@ __global__ __launch_bounds__(1024) void verify_scan_kernel(const int32_t* __rest
 // block_offset != NULL: the offsets come from verify_scan_kernel.  block_offset == NULL: every
 // block sums the counts of the blocks before it itself (cheap up to a few thousand blocks) and
 // the last block writes the grand total to out_count.
+template <int PER>
 __global__ __launch_bounds__(kVerifyThreads) void verify_scatter_kernel(
     const uint8_t* __restrict__ mask, int64_t n, const int64_t* __restrict__ block_offset,
-    const int32_t* __restrict__ block_count, int64_t* __restrict__ out_index,
+    const typename VerifyCount<PER>::type* __restrict__ block_count, int64_t* __restrict__ out_index,
     int64_t* __restrict__ out_count) {
   __shared__ int32_t wave_total[kVerifyThreads / 64];
   __shared__ int64_t wave_before[kVerifyThreads / 64];
@@ -320,12 +334,12 @@ __global__ __launch_bounds__(kVerifyThreads) void verify_scatter_kernel(
       *out_count = offset + block_count[blockIdx.x];
     if (!out_index) return;
   }
-  const int64_t base = ((int64_t)blockIdx.x * kVerifyThreads + threadIdx.x) * kPerThread;
+  const int64_t base = ((int64_t)blockIdx.x * kVerifyThreads + threadIdx.x) * PER;
   uint32_t bits = 0;
-  if (base + kPerThread <= n && (reinterpret_cast<uintptr_t>(mask) & 3) == 0) {
+  if (PER == 4 && base + PER <= n && (reinterpret_cast<uintptr_t>(mask) & 3) == 0) {
     bits = *reinterpret_cast<const uint32_t*>(mask + base);
   } else {
-    for (int j = 0; j < kPerThread; ++j)
+    for (int j = 0; j < PER; ++j)
       if (base + j < n) bits |= (uint32_t)(mask[base + j] & 1u) << (8 * j);
   }
   const int mine = __popc(bits);
@@ -340,7 +354,7 @@ __global__ __launch_bounds__(kVerifyThreads) void verify_scatter_kernel(
   int64_t pos = offset + incl - mine;
   for (int w = 0; w < wave; ++w) pos += wave_total[w];
 #pragma unroll
-  for (int j = 0; j < kPerThread; ++j)
+  for (int j = 0; j < PER; ++j)
     if ((bits >> (8 * j)) & 1u) out_index[pos++] = base + j;
 }
 
@@ -611,7 +625,6 @@ static int verify_launch(const nezha_itemset* set, const int32_t* codes, int64_t
   const int64_t blocks = (n + kVerifyBlock - 1) / kVerifyBlock;
   const size_t counts_bytes = ((size_t)blocks * sizeof(int32_t) + 15) & ~(size_t)15;
   // (the probe pass writes its block counts whether or not they are wanted afterwards)
-  int32_t* block_count = static_cast<int32_t*>(workspace);
   int64_t* block_offset = reinterpret_cast<int64_t*>(static_cast<char*>(workspace) + counts_bytes);
   Radix r;
   r.L = set->L;
@@ -623,27 +636,45 @@ static int verify_launch(const nezha_itemset* set, const int32_t* codes, int64_t
   // access, so it is left out of the view)
   SetView view{set->slots, set->n_buckets, nullptr, 0, 0};
   dim3 grid((unsigned)blocks), block(kVerifyThreads);
-  {
-  ProfileScope prof(kVerifyProbe, stream);
-  switch (set->L) {
-    case 3:
-      hipLaunchKernelGGL(verify_probe_kernel<3>, grid, block, 0, stream, codes, n, r, view,
-                         out_mask, block_count);
-      break;
-    case 4:
-      hipLaunchKernelGGL(verify_probe_kernel<4>, grid, block, 0, stream, codes, n, r, view,
-                         out_mask, block_count);
-      break;
-    default:
-      hipLaunchKernelGGL(verify_probe_kernel<0>, grid, block, 0, stream, codes, n, r, view,
-                         out_mask, block_count);
+#define LAUNCH_PROBE(PER, counts)                                                                    \
+  do {                                                                                               \
+    ProfileScope prof(kVerifyProbe, stream);                                                         \
+    switch (set->L) {                                                                                \
+      case 3:                                                                                        \
+        hipLaunchKernelGGL((verify_probe_kernel<3, PER>), grid, block, 0, stream, codes, n, r, view, \
+                           out_mask, counts);                                                        \
+        break;                                                                                       \
+      case 4:                                                                                        \
+        hipLaunchKernelGGL((verify_probe_kernel<4, PER>), grid, block, 0, stream, codes, n, r, view, \
+                           out_mask, counts);                                                        \
+        break;                                                                                       \
+      default:                                                                                       \
+        hipLaunchKernelGGL((verify_probe_kernel<0, PER>), grid, block, 0, stream, codes, n, r, view, \
+                           out_mask, counts);                                                        \
+    }                                                                                                \
+  } while (0)
+  if (n <= kVerifyOnePerLane) {
+    uint16_t* const counts = static_cast<uint16_t*>(workspace);
+    grid = dim3((unsigned)((n + kVerifyThreads - 1) / kVerifyThreads));
+    LAUNCH_PROBE(1, counts);
+    NEZHA_HIP_CHECK(hipGetLastError());
+    if (compact) {
+      ProfileScope prof(kVerifyScatter, stream);
+      hipLaunchKernelGGL(verify_scatter_kernel<1>, grid, block, 0, stream, (const uint8_t*)out_mask, n,
+                         (const int64_t*)nullptr, (const uint16_t*)counts, out_index, out_count);
+      NEZHA_HIP_CHECK(hipGetLastError());
+    }
+    return NEZHA_OK;
   }
-  }
+  int32_t* const block_count = static_cast<int32_t*>(workspace);
+  LAUNCH_PROBE(4, block_count);
+#undef LAUNCH_PROBE
+  static_assert(kPerThread == 4, "the probe pass's tuples per lane");
   NEZHA_HIP_CHECK(hipGetLastError());
   if (compact && blocks <= kFusedPrefixBlocks) {
     // few blocks: the scatter pass forms its own offsets, no separate scan launch
     ProfileScope prof(kVerifyScatter, stream);
-    hipLaunchKernelGGL(verify_scatter_kernel, grid, block, 0, stream, (const uint8_t*)out_mask, n,
+    hipLaunchKernelGGL(verify_scatter_kernel<4>, grid, block, 0, stream, (const uint8_t*)out_mask, n,
                        (const int64_t*)nullptr, (const int32_t*)block_count, out_index, out_count);
     NEZHA_HIP_CHECK(hipGetLastError());
   } else if (compact) {
@@ -655,7 +686,7 @@ static int verify_launch(const nezha_itemset* set, const int32_t* codes, int64_t
     NEZHA_HIP_CHECK(hipGetLastError());
     if (out_index) {
       ProfileScope prof(kVerifyScatter, stream);
-      hipLaunchKernelGGL(verify_scatter_kernel, grid, block, 0, stream,
+      hipLaunchKernelGGL(verify_scatter_kernel<4>, grid, block, 0, stream,
                          (const uint8_t*)out_mask, n, (const int64_t*)block_offset,
                          (const int32_t*)block_count, out_index, (int64_t*)nullptr);
     }
